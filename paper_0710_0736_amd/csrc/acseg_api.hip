@@ -242,10 +242,7 @@ Coefs coefs_of(const acseg_problem* p) {
         c.rhs.wd[k] = w[k] / D;
         c.rhs.wda[k] = (float)(w[k] / D * (1.0 / p->tau + 2.0 / p->eps));
     }
-    for (int k = 0; k < 4; ++k) {
-        c.rhs.wdr[k] = c.rhs.wd[k] / c.rhs.wd[0];
-        c.rhs.s1[k] = (float)(1.0 - (double)c.fine.kappa[k] * a[k]);
-    }
+    for (int k = 0; k < 4; ++k) c.rhs.wdr[k] = c.rhs.wd[k] / c.rhs.wd[0];
     c.fine.e2 = (float)e2;
     c.rhs.a = 1.0 / p->tau + 2.0 / p->eps;
     c.rhs.lambda = p->lambda;

@@ -72,7 +72,6 @@ struct RhsCoef {
     double lambda;
     double wdr[4];  // wd of the class over wd[0]
     float wda[4];   // (w / D)(1/tau + 2/eps) per node class (< 1 when eps > 0.71 h)
-    float s1[4];    // 1 - kappa sum_q c_pq: the sum over the phases of a node's rhs'
 };
 
 constexpr int kCmeansBlocks = 1024;  // workgroups of the colour-mean pass (every CU busy)
