@@ -231,19 +231,22 @@ __device__ __forceinline__ void adj_sweeps(AdjTile<N, C>& t, const AdjArgs& a, i
         nk[r][e] = k;
         rk[r][e] = k >= 2.f ? 1.f / k : 0.f;
     });
-    // weights of the lane's nodes (0 outside the lattice)
-    [[maybe_unused]] float kh[2][2], kv[2][2];
+    // coupling and edge weights of the lane's nodes (0 outside the lattice)
+    [[maybe_unused]] float kp[2][2], wh[2], wv[2];
     const float k0 = uniform_f(a.coef.kappa[0]);
     if constexpr (!INT) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            wh[q] = edge_w_h(gy + q, H);
+            wv[q] = edge_w_v(gx + q, W);
+        }
 #pragma unroll
         for (int r = 0; r < 2; ++r)
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
                 const int x = gx + e, y = gy + r;
                 const bool in = x >= 0 && x < W && y >= 0 && y < H;
-                const float k = in ? sel4(a.coef.kappa, node_class(x, y, W, H)) : 0.f;
-                kh[r][e] = k * edge_w_h(y, H);
-                kv[r][e] = k * edge_w_v(x, W);
+                kp[r][e] = in ? sel4(a.coef.kappa, node_class(x, y, W, H)) : 0.f;
             }
     }
     // rows exchanged between groups, two buffers: slot g + 1 of `bot` is group g's
@@ -283,7 +286,8 @@ __device__ __forceinline__ void adj_sweeps(AdjTile<N, C>& t, const AdjArgs& a, i
                     side = dpp_move_f<0x130>(z[r][0][i]);  // wave_shl:1
                 const float hs = z[r][1 - e][i] + side;
                 const float vs = z[1 - r][e][i] + (r == 0 ? up[i] : dn[i]);
-                v[i] = INT ? fmaf(k0, hs + vs, b[r][e][i]) : fmaf(kh[r][e], hs, fmaf(kv[r][e], vs, b[r][e][i]));
+                // the edge weights are powers of two: every tile rounds a node alike
+                v[i] = INT ? fmaf(k0, hs + vs, b[r][e][i]) : fmaf(kp[r][e], fmaf(wh[r], hs, wv[e] * vs), b[r][e][i]);
             }
             // T_p
             auto masked = [&](int i, float w) __attribute__((always_inline)) {
@@ -424,6 +428,8 @@ __global__ __launch_bounds__(kBlock) void k_adj_check(AdjArgs a, int sweeps) {
 // hence at most 768 of them; four spill (23.7 us).
 template <int N, int C>
 __global__ __launch_bounds__(kBlock, (N * C <= 12 ? 3 : 2)) void k_adj_accum(AdjArgs a) {
+    // both nodes of a pair round alike: only the multiply-adds that are written as such are fused
+#pragma clang fp contract(off)
     constexpr int Q = 3 + N * C;
     constexpr int T = kBlock;
     __shared__ double sh[Q][T];
@@ -501,21 +507,20 @@ __global__ __launch_bounds__(kBlock, (N * C <= 12 ? 3 : 2)) void k_adj_accum(Adj
                 const float z = zv[0][e][i], un = unv[0][e][i], u1 = u1v[0][e][i];
                 const float l = e == 0 ? (x > 0 ? lf[i] : 0.f) : u1v[0][0][i];
                 const float r = e == 0 ? u1v[0][1][i] : (x + 2 < W ? rt[i] : 0.f);
-                const float Au1 = ast * u1 - (wh * (l + r) + wv * (up[0][e][i] + dn[0][e][i]));
-                const float zM = z * Mp;
+                const float Au1 = fmaf(ast, u1, -fmaf(wh, l + r, wv * (up[0][e][i] + dn[0][e][i])));
+                const float zM = z * Mp, lz = lam2 * zM;
                 float F = 0.f;
 #pragma unroll
                 for (int k = 0; k < C; ++k) {
                     const float d = Ik[0][e][k] - c[i * C + k];
                     F = fmaf(d, d, F);
-                    const float g = lam2 * zM * d;
-                    tq[3 + i * C + k] += g;
-                    ib[0][e][k] -= g;
+                    tq[3 + i * C + k] = lz * d;
+                    ib[0][e][k] = fmaf(-lz, d, ib[0][e][k]);
                     if (share) ib[0][e][k] = fmaf(w * cmA[i * C + k], u1, ib[0][e][k]);
                 }
                 ubo[0][e][i] = aa * zM;
                 tq[0] = fmaf(zM, F, tq[0]);
-                tq[1] += z * fmaf(ce * Mp, un, -Au1);
+                tq[1] = fmaf(z, fmaf(ce * Mp, un, -Au1), tq[1]);
                 tq[2] = fmaf(zM, u1 - un, tq[2]);
             }
 #pragma unroll
