@@ -598,11 +598,14 @@ acseg_status run_steps(acseg_ctx* ctx, const acseg_problem* p, const Ctl* ctl, i
         window = std::min(2 * window, kMaxWindow);
         const int f = ctx->host_ctl->steps_done;
         if (f < n + m) {
-            // step f needs more: a little more where the guess came from its
-            // predecessors, else half as many again
-            for (int k = guess; ctx->host_ctl->steps_done == f;) {
+            // step f needs more: first a little more where the guess came from its
+            // predecessors, half as many again for a call's first step; twice that
+            // with every further read, up to 64 (a step may need far more than the
+            // ones before it: from 2 to 80 cycles in 8 reads)
+            int more = f > 0 ? std::max(1, guess / 8) : (guess + 1) / 2;
+            for (int k = guess; ctx->host_ctl->steps_done == f; more = std::max(more, std::min(2 * more, 64))) {
                 if (k >= p->max_cycles) return ACSEG_ERR_HIP;  // its last end does not block
-                const int end = std::min(p->max_cycles, k + (f > 0 ? std::max(1, k / 8) : (k + 1) / 2));
+                const int end = k + std::min(p->max_cycles - k, more);
                 ACSEG_TRY(launch_unblock(const_cast<Ctl*>(ctl), f & 1, s));
                 if ((v = step(f, k, end)) != ACSEG_OK || (v = after(f)) != ACSEG_OK || (v = read()) != ACSEG_OK) return v;
                 k = end;
