@@ -357,9 +357,10 @@ acseg_status acseg_solve(acseg_ctx *ctx, const acseg_problem *p, const float *im
  * static device memory: ACSEG_NO_ALLOC_SCRATCH_BYTES (80 MiB) on every device
  * the library runs on, reserved when the library's code is loaded there and
  * held until the process ends.  It calls no device or host allocator.
- * Problems whose workspace (acseg_workspace_size) exceeds the scratch are
- * refused with ACSEG_ERR_TOO_LARGE before anything is enqueued; 1024 x 1024 at
- * N = 4 fits with its full multigrid hierarchy.  Every call on one device
+ * Problems whose workspace (acseg_workspace_size) exceeds the scratch by more
+ * than 1 MiB, which is held for it beside, are refused with
+ * ACSEG_ERR_TOO_LARGE before anything is enqueued; 1024 x 1024 at N = 4 fits
+ * with its full multigrid hierarchy.  Every call on one device
  * uses that device's one scratch array and leaves its contents behind (each
  * call initialises what it reads): calls that can overlap on one device --
  * other streams, other threads, other contexts -- race and must be
