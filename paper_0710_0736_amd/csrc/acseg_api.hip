@@ -1301,7 +1301,10 @@ acseg_status acseg_solve_batched(acseg_ctx* ctx, int32_t B, const acseg_problem*
 
     // ---- results
     ACSEG_TRY(per_launch([&](const BatchGroup& g, int i0, int cnt, const BatchMeans& out) {
-        return launch_batch_results(g.N, g.C, dimg, dimgs + g.img0 + i0, cnt, out, 128, p0.steps, fixed_c ? 1 : 0, s);
+        int64_t most = 0;
+        for (int i = i0; i < i0 + cnt; ++i)
+            most = std::max(most, (int64_t)g.N * ps[g.members[i]].W * ps[g.members[i]].H);
+        return launch_batch_results(g.N, g.C, dimg, dimgs + g.img0 + i0, cnt, out, most, p0.steps, fixed_c ? 1 : 0, s);
     }));
     if (stats)
         for (int b = 0; b < B; ++b) {

@@ -129,9 +129,10 @@ struct BatchMeans {
 // of any image of the group.
 hipError_t launch_batch_means(int N, int C, const BatchImage* d, const int* imgs, int nimg, const BatchMeans& out,
                               int blocks, int steps, int fixed_c, hipStream_t s);
-// After it: every field into the caller's buffer, and its means into c_out.
+// After it: every field into the caller's buffer, and its means into c_out.  most: values
+// of the largest field of the group.
 hipError_t launch_batch_results(int N, int C, const BatchImage* d, const int* imgs, int nimg, const BatchMeans& out,
-                              int blocks, int steps, int fixed_c, hipStream_t s);
+                                int64_t most, int steps, int fixed_c, hipStream_t s);
 
 // ---- launchers (kernels_cycle.hip) ---------------------------------------
 
