@@ -390,8 +390,10 @@ struct EnergyArgs {
 
 // Four nodes per thread and access, as k_cmeans; the lower neighbours come from a
 // second read of the next row (cache).  1920 x 1080, N = 4: 34 -> 28 us.
+// (N = 8, C = 4 needs the bound: free of it the compiler takes 257 registers, which leaves
+// one wave per SIMD: 4096^2 927 us with one node per access, 1020 so, 705 with two waves.)
 template <int N, int C>
-__global__ __launch_bounds__(kBlock) void k_energy(EnergyArgs a) {
+__global__ __launch_bounds__(kBlock, (N * C >= 32 ? 2 : 1)) void k_energy(EnergyArgs a) {
     __shared__ double cs[N * C];
     __shared__ double sh[kBlock / kWave][3];
     if (threadIdx.x < N * C) cs[threadIdx.x] = a.c64[threadIdx.x];
