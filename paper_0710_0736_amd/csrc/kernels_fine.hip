@@ -434,7 +434,9 @@ __global__ __launch_bounds__(kBlock, (N * C >= 32 ? 2 : 1)) void k_energy(Energy
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const double uj = (double)v[j];
-                const double dh = uj - (double)v[j + 1], dv = uj - (double)d[j];
+                // (selected, not weighted by 0: an infinite value has no edge past the lattice)
+                const double dh = ch[j] != 0.0 ? uj - (double)v[j + 1] : 0.0;
+                const double dv = cv[j] != 0.0 ? uj - (double)d[j] : 0.0;
                 e0 = fma(ch[j] * dh, dh, e0);
                 e0 = fma(cv[j] * dv, dv, e0);
                 const double wu = w[j] * uj;

@@ -40,3 +40,13 @@ def test_energy_matches_float64(N, C, W, H):
     e = acseg.energy(p, torch.from_numpy(image).cuda(), torch.from_numpy(u).cuda()).cpu().numpy()
     # sums of up to 16 nodes per thread and then a tree, in float64; only e[1] has terms of both signs (none here)
     assert np.allclose(e, reference(p, image.astype(np.float64), u.astype(np.float64)), rtol=1e-12, atol=0)
+
+
+@pytest.mark.parametrize("x,y", [(4, 2), (0, 2), (2, 4), (3, 0), (4, 4), (0, 0)])
+def test_infinite_value_at_the_boundary(x, y):
+    """Its edges inside the lattice make the interface part infinite; there is none beyond."""
+    u = torch.full((2, 5, 5), 0.5)
+    u[0, y, x] = float("inf")
+    p = acseg.Problem(H=5, W=5, C=1, N=2, h=1.0, eps=1.0, tau=1.0, lam=1.0)
+    e = acseg.energy(p, torch.rand((1, 5, 5)).cuda(), u.cuda())
+    assert torch.isposinf(e[0]), e
