@@ -49,9 +49,9 @@ HBM_PEAK_GBS = 8000.0
 # sweeps per cycle); must be re-measured whenever the kernel changes (absent:
 # null).
 TRAFFIC = {
-    ("voronoi1024_n4", 8, 1, 1, 2): 383.87e6,
+    ("voronoi1024_n4", 8, 1, 1, 2): 383.98e6,
     ("voronoi1024_n4", 1, 1, 1, 2): 51.38e6,
-    ("voronoi4096_n8", 1, 1, 1, 2): 1452.29e6,
+    ("voronoi4096_n8", 1, 1, 1, 2): 1457.08e6,
 }
 
 

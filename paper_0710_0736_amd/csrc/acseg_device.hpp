@@ -165,9 +165,11 @@ template <> struct SortNet<8> {
 // them well conditioned for inputs of any magnitude.  The sweep of the solver
 // calls it with CENTRED = false: its largest component is of order one (the
 // right-hand side, shifted per node so that its largest component lies in
-// [0, (w/D)(1/tau + 2/eps)], plus neighbour terms in [0, 1)), so every
-// component that can be free lies within one of it, and the plain sums are
-// as well conditioned.
+// [0, (w/D)(1/tau + 2/eps)], plus the neighbours' share, in [0, 1) where they are on the
+// simplex), so every component that can be free lies within one of it, and the plain sums
+// are as well conditioned.  The bound of the right-hand side is below one for eps > 0.71 h
+// and grows as h/eps below that, and with the sums of a start off the simplex: the result's
+// error is then that many roundings.
 // Components of the result lie in [0, 1], so max(v_i - theta, 0) is a clamp
 // to [0, 1], which folds into the subtraction.
 __device__ __forceinline__ float clamp01(float x) { return __builtin_amdgcn_fmed3f(x, 0.f, 1.f); }

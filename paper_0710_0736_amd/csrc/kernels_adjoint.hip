@@ -250,8 +250,8 @@ __device__ __forceinline__ void adj_sweeps(AdjTile<N, C>& t, const AdjArgs& a, i
             }
     }
     // rows exchanged between groups, two buffers: slot g + 1 of `bot` is group g's
-    // second row, slot g of `top` its first; the outermost slots are never written and
-    // only reach nodes that are dropped
+    // second row, slot g of `top` its first.  The outermost slots are filled once, below, with the
+    // group's own rows: they only reach nodes of the dropped rings, but are read
     constexpr int kRow = 32 * NPD, kBuf = 2 * (kAdjG + 1) * kRow;
     float* const bot_w = lds + (g + 1) * kRow + l * NPD;
     float* const bot_r = lds + g * kRow + l * NPD;
@@ -425,7 +425,8 @@ __global__ __launch_bounds__(kBlock) void k_adj_check(AdjArgs a, int sweeps) {
 // Two nodes per thread, every load that does not need the stopping rule before it: at
 // 512^2, N = 4, 12.5 -> 10.7 us (33 MB); the rows above and below in an XCD's own L2
 // make 1 us of that.  Registers hold three workgroups of 256 threads per CU at N = 4,
-// hence at most 768 of them; four spill (23.7 us).
+// hence at most 768 of them; four spill (23.7 us).  Above 12 sums two fit, and only N = 8, C = 4
+// spills there (92 registers; 512^2, five steps back: 1357 us before the register tiles, 1077 now).
 template <int N, int C>
 __global__ __launch_bounds__(kBlock, (N * C <= 12 ? 3 : 2)) void k_adj_accum(AdjArgs a) {
     // both nodes of a pair round alike: only the multiply-adds that are written as such are fused
